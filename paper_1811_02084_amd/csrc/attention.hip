@@ -441,7 +441,10 @@ __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, false
   f32x16 o[kBlk];
 #pragma unroll
   for (int i = 0; i < kBlk; ++i) o[i] = zero16();
-  float m2 = -INFINITY, lsum = 0.f;  // running max (log2 units) and row sum
+  // Running max (log2 units) and row sum.  The maximum starts finite: a tile (of this wave's group) whose
+  // logits of a row have all overflowed to -inf leaves it alone and adds exp2(-inf) = 0, where a start at
+  // -inf would make -inf + inf = NaN of it.
+  float m2 = -__FLT_MAX__, lsum = 0.f;
   const float c2 = fmaxf(fabsf(a.scale) * kLog2e, 1e-30f);
 
   auto process = [&](int t, const char* st) {
@@ -504,8 +507,7 @@ __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, false
     mx = fmaxf(mx, __shfl_xor(mx, 32));  // the other half-wave holds the rest of this query's row
     mx *= c2;  // c2 > 0, so a fully hidden row stays at -inf
     constexpr float kSlack = 8.f;
-    // first tile: m2 = -inf, always taken; some position is visible to every row (with groups: row blocks
-    // and a group's tiles are both 32 rows, so a row sees at least the first position of any tile it gets)
+    // taken on the first tile with a finite logit
     if (__builtin_expect(__any(mx > m2 + kSlack), 0)) {
       const float m_new = fmaxf(m2, mx);
       const float alpha = __builtin_amdgcn_exp2f(m2 - m_new);
@@ -575,7 +577,7 @@ __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, false
   }
   if constexpr (KVS > 1) {
     // the groups' softmax statistics: each part was taken against its own running maximum (a group that
-    // got no tile: -inf and a sum of 0, so its weight is 0)
+    // got no tile, or none with a finite logit: the lowest maximum and a sum of 0)
     constexpr int RW = NWAVES / KVS;
     __shared__ float stat_m[NWAVES * 32], stat_l[NWAVES * 32];
     if (hf == 0) {

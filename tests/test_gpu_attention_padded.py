@@ -55,6 +55,33 @@ def test_against_oracle(case):
         assert m2(got.float().cpu().numpy(), ref.data) <= TOL, name
 
 
+@pytest.mark.parametrize("case", [
+    (1, 200, 2, 64, False), (1, 200, 2, 64, True), (1, 200, 2, 96, False), (1, 200, 2, 128, False),   # waves in groups
+    (1, 200, 2, 128, True), (2, 200, 3, 256, False), (2, 200, 3, 256, True),
+    (5, 200, 32, 64, False), (5, 193, 16, 128, False), (5, 200, 16, 256, False)],                     # no groups
+    ids=lambda c: "-".join(map(str, c)))
+def test_logits_that_overflow(case):
+    """Whole tiles of memory rows whose logits are below the fp32 range (-inf) get no weight, wherever the
+    tile falls among the groups; exact powers of two on q and k, so the tolerance is the same."""
+    b, l, h, dk, causal = case
+    print(f"attention core, overflowing logits {case}", flush=True)
+    q, k, v, dctx = (mtf_inputs.normal(57, i, (b, l, h, dk)) for i in range(4))
+    q = ((q.float().abs() + 1).bfloat16().float() * 2.0**66).bfloat16()
+    k = (k.float() * 2.0**-66).bfloat16()
+    for lo, hi in [(32, 64), (96, 128)] if causal else [(0, 64), (96, 128)]:
+        k[:, lo:hi] = -(2.0**66)
+    scale = 1.0 / dk
+    qn, kn, vn = to_nt(q, (B, L, H, K)), to_nt(k, (B, M, H, K)), to_nt(v, (B, M, H, V))
+    ctx_ref, lse_ref = OL.attention_core_fwd(qn, kn, vn, scale, causal)
+    ctx, lse = mtf.attention_fwd(q.cuda(), k.cuda(), v.cuda(), scale, causal)
+    assert m2(ctx.float().cpu().numpy(), ctx_ref.data) <= TOL
+    assert np.max(np.abs(lse.cpu().numpy() - lse_ref.data)) <= 1e-3 * max(1.0, np.max(np.abs(lse_ref.data)))
+    refs = OL.attention_core_bwd(qn, kn, vn, ctx_ref, lse_ref, to_nt(dctx, (B, L, H, V)), scale, causal)
+    gots = mtf.attention_bwd(q.cuda(), k.cuda(), v.cuda(), ctx, lse, dctx.cuda(), scale, causal)
+    for name, got, ref in zip(("dq", "dk", "dv"), gots, refs):
+        assert m2(got.float().cpu().numpy(), ref.data) <= TOL, name
+
+
 def test_unfused_widths_remain():
     """A width above 128 other than 256 still runs the two einsums with the row softmax between."""
     q = mtf_inputs.normal(54, 0, (2, 72, 3, 136)).cuda()
