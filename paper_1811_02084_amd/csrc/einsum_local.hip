@@ -4,6 +4,7 @@
 // other legal request runs on fp32 FMAs: fp32 contractions of that form through LDS tiles, the rest on a
 // generic kernel (one thread per output element).
 #include "device_common.h"
+#include "einsum_folded_rule.h"
 #include "gemm_bf16.h"
 #include "timing.h"
 
@@ -315,11 +316,6 @@ int launch_generic(const void* a, const Dims& da, const void* b, const Dims* db,
 // Runs an fp32 contraction that as_gemm() folded.  Tiles of 16 x 16 while 64 x 64 ones would leave most
 // CUs idle: 768x512x256 (1536 of 16 x 16, 96 of 64 x 64) 21.0 against 33.0 us, 1024x768x256 (3072, 192)
 // 33.6 on 64 x 64.
-bool folded_supported(const GemmDesc& d) {
-  return d.M <= INT32_MAX / 2 && d.N <= INT32_MAX / 2 && d.K[0] <= INT32_MAX / 2 && d.batch0 * d.batch1 <= 65535 &&
-         ceil_div(d.M, 16) * ceil_div(d.N, 16) <= INT32_MAX / 2;
-}
-
 template <typename OutT>
 int launch_folded(const GemmDesc& d, const void* a, const void* b, int epi, const void* aux, int64_t bias_extent,
                   hipStream_t stream) {
@@ -473,7 +469,7 @@ int route_einsum(const void* a, const mtf_shape* a_local, const void* b, const m
   if (in_dt == MTF_F32 && r->has_b) {
     GemmDesc& d = r->gemm;
     bool swapped = false;
-    if (as_gemm(c, &d, &swapped) && folded_supported(d)) {
+    if (as_gemm(c, &d, &swapped) && folded_fits(d.M, d.N, d.K[0], d.batch0 * d.batch1)) {
       r->operand_a = swapped ? b : a;
       r->operand_b = swapped ? a : b;
       d.C = out;
