@@ -313,11 +313,9 @@ int launch_generic(const void* a, const Dims& da, const void* b, const Dims* db,
   return launch_status("einsum_generic_kernel");
 }
 
-// Runs an fp32 contraction that as_gemm() folded.  Tiles of 16 x 16 while 64 x 64 ones would leave most
-// CUs idle: 768x512x256 (1536 of 16 x 16, 96 of 64 x 64) 21.0 against 33.0 us, 1024x768x256 (3072, 192)
-// 33.6 on 64 x 64.
+// Runs an fp32 contraction that as_gemm() folded on the tiles the rule chose (kFp32Tile16 or kFp32Tile64).
 template <typename OutT>
-int launch_folded(const GemmDesc& d, const void* a, const void* b, int epi, const void* aux, int64_t bias_extent,
+int launch_folded(const GemmDesc& d, Fp32Kernel kernel, const void* a, const void* b, int epi, const void* aux, int64_t bias_extent,
                   hipStream_t stream) {
   FoldedArgs g;
   g.M = (int)d.M; g.N = (int)d.N; g.K = (int)d.K[0];
@@ -332,17 +330,15 @@ int launch_folded(const GemmDesc& d, const void* a, const void* b, int epi, cons
   g.accumulate = d.accumulate ? 1 : 0;
   g.bias_extent = bias_extent;
   g.epi = epi;
-  const int64_t batch = d.batch0 * d.batch1, small = ceil_div(d.M, 16) * ceil_div(d.N, 16);
+  const int64_t batch = d.batch0 * d.batch1, tile = kernel == kFp32Tile16 ? 16 : 64;
+  g.tiles_n = (int)ceil_div(d.N, tile);
+  const dim3 grid((unsigned)(ceil_div(d.M, tile) * g.tiles_n), (unsigned)batch);
   const float *fa = static_cast<const float*>(a), *fb = static_cast<const float*>(b), *fx = static_cast<const float*>(aux);
   LaunchTimer timer("einsum_folded_kernel", 2.0 * batch * d.M * d.N * d.K[0], 0, stream);
-  if (small * batch <= 2048) {
-    g.tiles_n = (int)ceil_div(d.N, 16);
-    einsum_folded_kernel<OutT, 1, 128><<<dim3((unsigned)small, (unsigned)batch), 256, 0, stream>>>(fa, fb, static_cast<OutT*>(d.C), fx, g);
-  } else {
-    g.tiles_n = (int)ceil_div(d.N, 64);
-    einsum_folded_kernel<OutT, 4, 32><<<dim3((unsigned)(ceil_div(d.M, 64) * g.tiles_n), (unsigned)batch), 256, 0, stream>>>(
-        fa, fb, static_cast<OutT*>(d.C), fx, g);
-  }
+  if (kernel == kFp32Tile16)
+    einsum_folded_kernel<OutT, 1, 128><<<grid, 256, 0, stream>>>(fa, fb, static_cast<OutT*>(d.C), fx, g);
+  else
+    einsum_folded_kernel<OutT, 4, 32><<<grid, 256, 0, stream>>>(fa, fb, static_cast<OutT*>(d.C), fx, g);
   return launch_status("einsum_folded_kernel");
 }
 
@@ -421,7 +417,7 @@ struct EinsumRoute {
   Dims da, db, dout;
   bool has_b = false;
   bool use_gemm = false;
-  bool use_folded = false;  // fp32 operands that fold to a matrix product (operand_a / operand_b by role)
+  Fp32Kernel folded = kFp32Generic;  // the tiles of fp32 operands that fold to a matrix product (operand_a / _b by role)
   const void *operand_a = nullptr, *operand_b = nullptr;
   GemmDesc gemm;
 };
@@ -469,13 +465,13 @@ int route_einsum(const void* a, const mtf_shape* a_local, const void* b, const m
   if (in_dt == MTF_F32 && r->has_b) {
     GemmDesc& d = r->gemm;
     bool swapped = false;
-    if (as_gemm(c, &d, &swapped) && folded_fits(d.M, d.N, d.K[0], d.batch0 * d.batch1)) {
+    if (as_gemm(c, &d, &swapped)) {
       r->operand_a = swapped ? b : a;
       r->operand_b = swapped ? a : b;
       d.C = out;
       d.alpha = alpha;
       d.accumulate = accumulate != 0;
-      r->use_folded = true;
+      r->folded = fp32_kernel(d.M, d.N, d.K[0], d.batch0 * d.batch1, d.a_kcontig, d.b_kcontig);
     }
   }
   return MTF_OK;
@@ -492,12 +488,12 @@ extern "C" int mtf_einsum_local(const void* a, const mtf_shape* a_local, const v
     return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (r.use_gemm) return gemm_bf16_launch(r.gemm, s);
-  if (r.use_folded) {
+  if (r.folded != kFp32Generic) {
     const bool with_bias = epi == MTF_EPI_BIAS || epi == MTF_EPI_BIAS_RELU;
     const int64_t bias_extent = !with_bias ? 0 : r.dout.rank ? r.dout.size[r.dout.rank - 1] : 1;
     const int e = !with_bias ? epi : epi == MTF_EPI_BIAS_RELU ? MTF_EPI_RELU : MTF_EPI_NONE;
-    return out_dt == MTF_BF16 ? launch_folded<bf16_t>(r.gemm, r.operand_a, r.operand_b, e, aux, bias_extent, s)
-                              : launch_folded<float>(r.gemm, r.operand_a, r.operand_b, e, aux, bias_extent, s);
+    return out_dt == MTF_BF16 ? launch_folded<bf16_t>(r.gemm, r.folded, r.operand_a, r.operand_b, e, aux, bias_extent, s)
+                              : launch_folded<float>(r.gemm, r.folded, r.operand_a, r.operand_b, e, aux, bias_extent, s);
   }
   int64_t count = 0;
   if (!r.has_b && is_componentwise(r.da, r.dout, epi, &count))
