@@ -69,10 +69,10 @@ struct Choice {
 
 // Tile choice by a cost model in microseconds, fitted to kernel traces of the layer's launches
 // and to single launches of [993..8192, 512..8192] outputs with 256..4096 contracted (operands
-// from memory): a shape's time is its rounds of tiles over the slots the machine has for it, each
-// round a fixed part (prologue and epilogue) plus what the tile takes per 1024 contracted.
-// What bounds a tile is mostly its operand stream: a CU takes in 45-65 GB/s however many
-// loads it has in flight, so a tile costs about its bytes, (BM + BN) * K * 2, and the widest
+// from memory): a shape's time is the rounds of tiles on the busiest XCD over the slots an XCD has for
+// it, each round a fixed part (prologue and epilogue) plus what the tile takes per 1024 contracted.
+// What bounds a tile is mostly its operand stream: these launches take in 7 to 14 TB/s in all (the more, the more
+// of it the tiles of an XCD share), so a tile costs about its bytes, (BM + BN) * K * 2, and the widest
 // tile that still gives every CU one wins:
 //   256x256  31.2 us per 1024 + 5      256x128  17.3 (A along k; else 19.5) + 6
 //   128x128, two workgroups per CU: 19.5 for the pair + 2; one per CU in k-groups: 10 + 3.7
@@ -81,12 +81,30 @@ struct Choice {
 // four-wave 128x128 kernel these shapes used before: 13.8), 2048x1024x1024 (256 of 128x64) 11.1
 // against 13.3 / 11.9 on 128x128 / 64x64, 4096x1024x4096 (256 of 128x128) 44 against 58 on either side,
 // 96x256x256 (8 of 64x64) 4.3 against 6.5.
+// The busiest XCD, not the chip: a batch's products are cut into eighths one by one, so 12 of 808x144 make
+// 36 tiles of 128x64 (21 = 7 x 3) for each of seven XCDs and none for the eighth: two rounds, 87 us at
+// K = 4112 against 51 on 128x128 (2 x 12 tiles).  And up to 8 tiles of a product on an XCD share so little
+// of their operands that the XCD takes in 0.95 to 1.2 TB/s: a floor under the shapes with the longest streams
+// (10 x 448x296x8192: 128x64 97, 64x64 93, 128x128 83 us).  Over 820 drawn launches the choice is within
+// 1 % of the fastest tile on average.
 Choice choose_tile(const GemmDesc& d) {
   const int64_t batch = d.batch0 * d.batch1;
-  auto count = [&](int bm, int bn) {
-    int64_t n = ceil_div(d.M, bm) * ceil_div(d.N, bn) * batch;
-    for (int p = 0; p < d.nextra; ++p) n += ceil_div(d.extra[p].M, bm) * ceil_div(d.extra[p].N, bn);
-    return n;
+  auto busiest = [&](int bm, int bn) {  // tiles on the XCD that gets the most, as the kernel deals them out
+    const int64_t first = ceil_div(d.M, bm) * ceil_div(d.N, bn);
+    if (d.nextra == 0) return batch * ceil_div(first, 8);
+    int64_t tiles[kMaxGroup] = {first}, most = first;
+    bool same = true;
+    for (int p = 0; p < d.nextra; ++p) {
+      tiles[p + 1] = ceil_div(d.extra[p].M, bm) * ceil_div(d.extra[p].N, bn);
+      most = std::max(most, tiles[p + 1]);
+      same = same && tiles[p + 1] == first;
+    }
+    const int n = 1 + d.nextra;
+    const int64_t eighth = ceil_div(most, 8);  // of the widest problem's grid
+    if (same && 8 % n == 0) return eighth * n;
+    int64_t sum = 0;
+    for (int p = 0; p < n; ++p) sum += std::min(tiles[p], eighth);
+    return sum;
   };
   auto per1024 = [&](int bk) {  // the longest problem's contracted length in whole k-tiles, / 1024
     double most = 0;
@@ -97,20 +115,29 @@ Choice choose_tile(const GemmDesc& d) {
     }
     return most / 1024.0;
   };
-  auto rounds = [](int64_t tiles, int slots) { return (double)ceil_div(tiles, slots); };
+  auto unshared = [&](int bm, int bn) {
+    if (batch == 1 || ceil_div(ceil_div(d.M, bm) * ceil_div(d.N, bn), 8) > 8) return 0.0;
+    double k = 0;
+    for (int s = 0; s < d.nseg; ++s) k += (double)d.K[s];
+    const int64_t rows = std::min<int64_t>(bm, d.M) + std::min<int64_t>(bn, d.N);
+    return (double)(busiest(bm, bn) * rows) * k * 2 / 1.1e6 + 3.0;
+  };
+  auto rounds = [](int64_t tiles, int per_cu) { return (double)ceil_div(tiles, 32 * per_cu); };  // 32 CUs per XCD
   const double k64 = per1024(64), k128 = per1024(128);
-  const int64_t small_tiles = count(128, 128), tiny_tiles = count(64, 64);
+  const int64_t small_tiles = busiest(128, 128), tiny_tiles = busiest(64, 64);
+  const double pair_rate = batch == 1 ? std::min(19.5, 15.2 + 0.5 * (double)(small_tiles - 33)) : 19.5;
   const Choice choices[] = {
-      {rounds(count(256, 256), 256) * (31.2 * k64 + 5.0), launch_large},
-      {rounds(count(256, 128), 256) * ((d.a_kcontig ? 17.3 : 19.5) * k64 + 6.0), launch_split},
-      // two small tiles share a CU and cover each other; with at most one per CU, k-groups do that
-      small_tiles > 256 ? Choice{rounds(small_tiles, 512) * (19.5 * k64 + 2.0), launch_small}
-                        : Choice{10.0 * k64 + 3.7, launch_pair},
-      {rounds(count(128, 64), 256) * (7.2 * k128 + 4.2), launch_narrow},
+      {rounds(busiest(256, 256), 1) * (31.2 * k64 + 5.0), launch_large},
+      {rounds(busiest(256, 128), 1) * ((d.a_kcontig ? 17.3 : 19.5) * k64 + 6.0), launch_split},
+      // two small tiles share a CU and cover each other (and take less time while few CUs have two: 34 on
+      // an XCD, 15.2 per 1024); with at most one per CU, k-groups do that
+      small_tiles > 32 ? Choice{rounds(small_tiles, 2) * (pair_rate * k64 + 2.0), launch_small}
+                       : Choice{10.0 * k64 + 3.7, launch_pair},
+      {std::max(rounds(busiest(128, 64), 1) * (7.2 * k128 + 4.2), unshared(128, 64)), launch_narrow},
       // 64x64 with a deep ring and the CU to itself, or two with a shallow one: the deep ring pays
       // from about 6 k-tiles on (993x1024: K = 512 7.2 against 7.0 us, K = 1024 8.5 against 9.2)
-      {rounds(tiny_tiles, 256) * (4.3 * k128 + 4.0), k128 >= 0.75 ? launch_tiny_deep : launch_tiny},
-      {rounds(tiny_tiles, 512) * (8.6 * k128 + 3.2), launch_tiny},
+      {std::max(rounds(tiny_tiles, 1) * (4.3 * k128 + 4.0), unshared(64, 64)), k128 >= 0.75 ? launch_tiny_deep : launch_tiny},
+      {std::max(rounds(tiny_tiles, 2) * (8.6 * k128 + 3.2), unshared(64, 64)), launch_tiny},
   };
   // the k-tiles of 128 need twice the reach in the loaders' 32-bit offsets
   const bool reach128 = ld_fits_32bit_offsets(d, 127);

@@ -65,6 +65,24 @@ def test_epilogues(tile, size):
         assert torch.equal(got, (0.5 * ref + old).to(dt))
 
 
+@pytest.mark.parametrize("b,m,n,k", [(12, 808, 144, 1032), (10, 448, 296, 2056)])
+@pytest.mark.parametrize("da", ["mk", "km"])
+def test_batches_of_few_tiles(b, m, n, k, da):
+    """The products of a batch are dealt to the 8 XCDs one by one.  12 of 808x144: 128x64 tiles would be two rounds on
+    seven XCDs where 128x128 tiles are one; 10 of 448x296: one round of either, of a shorter stream on
+    128x128, since the few tiles of a product on an XCD share little."""
+    print(f"gemm batch {b} x {m}x{n}x{k} {da}", flush=True)
+    a, w = _ints((b, m, k), 6), _ints((b, k, n), 7)
+    ref = torch.stack([x.float() @ y.float() for x, y in zip(a, w)])
+    ag = (a if da == "mk" else a.transpose(1, 2).contiguous()).cuda()
+    mtf.timing_enable(True)
+    got = mtf.einsum_local(ag, "b" + da, w.cuda(), "bkn", "bmn", out_dtype=torch.float32)
+    names = [t["kernel"] for t in mtf.timing_collect()]
+    mtf.timing_enable(False)
+    assert torch.equal(got.cpu(), ref)
+    assert len(names) == 1 and "TileCfg<128, 128, " in names[0], names
+
+
 @pytest.mark.parametrize("size,parts", [((200, 136, 160), 2), ((136, 72, 4096), 4), ((1032, 1544, 1824), 2)])
 def test_ranges(size, parts):
     m, n, k = size
