@@ -131,8 +131,9 @@ Choice choose_tile(const GemmDesc& d) {
       {rounds(busiest(256, 128), 1) * ((d.a_kcontig ? 17.3 : 19.5) * k64 + 6.0), launch_split},
       // two small tiles share a CU and cover each other (and take less time while few CUs have two: 34 on
       // an XCD, 15.2 per 1024); with at most one per CU, k-groups do that
+      // (from 448 contracted on: below, their exchange costs more: 4096x1024x256 9.7 us against 8.8)
       small_tiles > 32 ? Choice{rounds(small_tiles, 2) * (pair_rate * k64 + 2.0), launch_small}
-                       : Choice{10.0 * k64 + 3.7, launch_pair},
+                       : Choice{10.0 * k64 + 3.7, k64 > 448 / 1024.0 ? launch_pair : launch_small},
       {std::max(rounds(busiest(128, 64), 1) * (7.2 * k128 + 4.2), unshared(128, 64)), launch_narrow},
       // 64x64 with a deep ring and the CU to itself, or two with a shallow one: the deep ring pays
       // from about 6 k-tiles on (993x1024: K = 512 7.2 against 7.0 us, K = 1024 8.5 against 9.2)

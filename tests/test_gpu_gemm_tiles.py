@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 TILES = {"TileCfg<64, 64, 1, 1, 4, 128, 8, 2>": [(200, 136, 136), (8, 8, 8), (1, 72, 264)],
          "TileCfg<64, 64, 1, 1, 4, 128, 8, 4>": [(200, 136, 776), (65, 56, 1032)],
          "TileCfg<128, 64, 2, 1, 4, 128, 8, 3>": [(1032, 1544, 904)],
-         "TileCfg<128, 128, 2, 2, 2, 64, 8, 4>": [(2056, 1544, 200)]}
+         "TileCfg<128, 128, 2, 2, 2, 64, 8, 4>": [(2056, 1544, 520)],
+         "TileCfg<128, 128, 2, 2, 1, 64, 8, 2>": [(2056, 1544, 200)]}
 CASES = [(tile, size) for tile, sizes in TILES.items() for size in sizes]
 
 
