@@ -1203,7 +1203,9 @@ int attn_fwd_launch(const AttnShape& s, const bf16_t* q, const bf16_t* k, const 
   const double pairs = s.causal ? 0.5 * s.length * (s.length + 1.0) : (double)s.length * s.length;
   const double flops = 2.0 * 2.0 * s.batch * s.heads * pairs * s.head_dim;
   const double bytes = 4.0 * s.batch * s.length * s.heads * s.head_dim * 2;
-  if (s.head_dim == 256 && wave_groups(s, false).kvs != 0) {
+  // a single 32-row tile of memory leaves nothing to divide: 1 x 8, 16 heads of 256 8.6 us with groups, 8.0
+  // without (the backward kernels still gain from the second pair of waves, which share their loads)
+  if (s.head_dim == 256 && s.length > 32 && wave_groups(s, false).kvs != 0) {
     LaunchTimer timer("attn_fwd_kernel<256, 4, false, 2>", flops, bytes, stream);
     attn_fwd_kernel<256, 4, false, 2><<<row_block_grid(s, 2), 256, 0, stream>>>(a);
     return launch_status("attn_fwd_kernel");

@@ -82,6 +82,17 @@ def test_logits_that_overflow(case):
         assert m2(got.float().cpu().numpy(), ref.data) <= TOL, name
 
 
+@pytest.mark.parametrize("length,kernel", [(8, "attn_fwd_kernel<256, 2, false, 1>"), (32, "attn_fwd_kernel<256, 2, false, 1>"),
+                                           (33, "attn_fwd_kernel<256, 4, false, 2>")])
+def test_one_tile_of_memory_needs_no_groups(length, kernel):
+    q = mtf_inputs.normal(58, 0, (1, length, 2, 256)).cuda()
+    mtf.timing_enable(True)
+    mtf.attention_fwd(q, q, q, 0.1, True)
+    names = [t["kernel"] for t in mtf.timing_collect()]
+    mtf.timing_enable(False)
+    assert names == [kernel]
+
+
 def test_unfused_widths_remain():
     """A width above 128 other than 256 still runs the two einsums with the row softmax between."""
     q = mtf_inputs.normal(54, 0, (2, 72, 3, 136)).cuda()
