@@ -51,8 +51,9 @@ __global__ void __launch_bounds__(256) embedding_kernel(const int32_t* __restric
 // a block are compacted in ascending order with ballots; a thread owns 8 columns per pass).  What
 // bounds it is the scan, a chain of loads and barriers in every workgroup: eight loads in flight and one
 // barrier per 1024 ids when none of them hits: 4096 tokens of width 1024 into 2048 rows 14.4 -> 8.5 us,
-// 8192 24.1 -> 12.7.  kScan = ids per thread and block; 1 for calls of at most 128 ids, where the other
-// seven loads fetch nothing (64 tokens: 4.9 against 5.6 us).
+// 8192 24.1 -> 12.7.  kScan = ids per thread and block: as few as cover a call of up to 512 ids in one block,
+// where the other loads fetch nothing (64 tokens: 1 4.9 us, 8 5.6; 256 tokens of width 64 into 8192 rows: 1 5.6,
+// 2 5.5, 4 5.8, 8 7.1; 512: 1 6.9, 2 6.1, 4 5.8, 8 7.1).
 template <int kScan>
 __global__ void __launch_bounds__(128) embedding_grad_kernel(const int32_t* __restrict__ ids,
                                                             const bf16_t* __restrict__ de, float* __restrict__ dtable,
@@ -224,6 +225,10 @@ int mtf_embedding_grad_local(const void* ids, int64_t count, const void* de, int
   };
   if (count <= 128)
     launch(embedding_grad_kernel<1>);
+  else if (count <= 256)
+    launch(embedding_grad_kernel<2>);
+  else if (count <= 512)
+    launch(embedding_grad_kernel<4>);
   else
     launch(embedding_grad_kernel<8>);
   return launch_status("embedding_grad_kernel");

@@ -1,5 +1,5 @@
 """The layer-normalisation gradients and the embedding gradient at the sizes where their passes end
-raggedly: rows not a multiple of a workgroup's waves, every chunk count of d_model, blocks of 1024 ids."""
+raggedly: rows not a multiple of a workgroup's waves, every chunk count of d_model, blocks of 128 to 1024 ids."""
 import pytest
 import torch
 
@@ -31,7 +31,7 @@ def test_layer_norm_gradients(rows, d):
     assert ((dgain.double().cpu() - (dy.double() * xh).sum(0)).abs() <= (rows + 8) * 2.0**-24 * terms + 1e-30).all()
 
 
-@pytest.mark.parametrize("count", [0, 1, 127, 128, 129, 1023, 1024, 1025, 5000])
+@pytest.mark.parametrize("count", [0, 1, 127, 128, 129, 256, 257, 512, 513, 1023, 1024, 1025, 5000])
 @pytest.mark.parametrize("d", [8, 1024, 1032])
 def test_embedding_gradient_exact(count, d):
     """Small integers; a row that no token hits, one that most do, ids outside the stripe."""
