@@ -1,7 +1,7 @@
 """The fused attention kernels at head widths 64, 128 and 256, and every other multiple of 8 up to 128
 padded to 64 or 128 in LDS, at the edges of tiles, row blocks and workgroup sizes, with and without the
-waves in groups over the memory (query) rows, against the oracle (same tolerance as in the
-widths' own test: bf16 storage, fp32 accumulation)."""
+waves in groups over the memory (query) rows, and the unfused formulation at widths no fused kernel
+takes, against the oracle (same tolerance as in the widths' own test: bf16 storage, fp32 accumulation)."""
 import math
 
 import numpy as np
@@ -33,12 +33,17 @@ CASES = [  # batch, length, heads, d_k, causal, scale (None: 1/sqrt(d_k))
     (4, 384, 32, 64, True, None), (4, 328, 32, 48, False, None), (4, 328, 32, 104, True, None),   # 8 waves
     (2, 104, 2, 64, True, -0.05), (2, 104, 2, 40, True, -0.05), (2, 104, 2, 96, False, -0.05),
 ]
+UNFUSED = [  # widths above 128 other than 256: the two einsums with a row softmax between them, batched products
+    (2, 72, 3, 136, True, None), (2, 136, 3, 136, False, None), (1, 200, 2, 264, True, None), (3, 72, 2, 248, False, -0.05),
+    (2, 104, 2, 136, True, -0.05), (1, 328, 4, 192, True, None), (1, 8, 1, 520, False, None),
+]
 
 
-@pytest.mark.parametrize("case", CASES, ids=["-".join(map(str, c)) for c in CASES])
+@pytest.mark.parametrize("case", CASES + UNFUSED, ids=["-".join(map(str, c)) for c in CASES + UNFUSED])
 def test_against_oracle(case):
     b, l, h, dk, causal, scale = case
     print(f"attention core {case}", flush=True)
+    mtf.timing_enable(True)
     scale = 1.0 / math.sqrt(dk) if scale is None else scale
     q, k, v, dctx = (mtf_inputs.normal(53, i, (b, l, h, dk)) for i in range(4))
     qn, kn, vn = to_nt(q, (B, L, H, K)), to_nt(k, (B, M, H, K)), to_nt(v, (B, M, H, V))
@@ -53,6 +58,9 @@ def test_against_oracle(case):
     gots = mtf.attention_bwd(q.cuda(), k.cuda(), v.cuda(), ctx_s.cuda(), lse_s.cuda(), dctx.cuda(), scale, causal)
     for name, got, ref in zip(("dq", "dk", "dv"), gots, refs):
         assert m2(got.float().cpu().numpy(), ref.data) <= TOL, name
+    names = [t["kernel"] for t in mtf.timing_collect()]
+    mtf.timing_enable(False)
+    assert any("softmax" in n for n in names) == (case in UNFUSED), names
 
 
 @pytest.mark.parametrize("case", [

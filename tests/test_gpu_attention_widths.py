@@ -1,6 +1,5 @@
 """The attention core behind mtf_attention_fwd / mtf_attention_bwd against the oracle: the fused
-kernels at head widths 128 and 256 (the paper's translation and language models), and at any other
-width two einsums on the GEMM kernel with a row softmax between them."""
+kernels at head widths 128 and 256 (the paper's translation and language models), 64, and 32 padded to 64."""
 import math
 
 import numpy as np
