@@ -188,6 +188,24 @@ def test_layer_head_width_256():
     _layer_case(mtf_inputs.layer_inputs(28, 2, 200, 256, 2, 256, 520, 32, 16384), True, "x[2,200,256] 2 heads of width 256")
 
 
+@pytest.mark.parametrize("dims", [(3, 131, 264, 2, 128, 520), (1, 331, 1032, 3, 128, 1048), (2, 70, 72, 2, 128, 136)])
+def test_layer_ragged_width_residual_in_the_epilogue(dims):
+    """d_model that no tile divides, at sizes whose residual adds all take place in the einsums' epilogues (no
+    launch that sums partial buffers)."""
+    b, l, dm, h, dk, f = dims
+    cfg = mtf_inputs.layer_inputs(30, *dims, 16 * h, 16 * f)
+    g = on_device(cfg)
+    w = {k: g[k] for k in WEIGHT_DIMS}
+    bufs = mtf.layer_alloc(g["x"], w)
+    mtf.timing_enable(True)
+    mtf.layer_fwd(g["x"], w, cfg["scale"], False, bufs)
+    mtf.layer_bwd(g["x"], w, bufs["saved"], g["dz"], cfg["scale"], False, bufs)
+    names = [t["kernel"] for t in mtf.timing_collect()]
+    mtf.timing_enable(False)
+    assert names and not any("reduce_partials" in n for n in names), names
+    _layer_case(cfg, False, f"x{list(dims[:3])} {h} heads of {dk}, d_ff {f}")
+
+
 def test_layer_config5_full_size():
     cfg = mtf_inputs.config5()
     _layer_case(cfg, cfg["causal"], "config 5", exact_gate=True)
