@@ -156,8 +156,9 @@ int mtf_slice_copy(void* full, void* slice, const mtf_shape* t, const mtf_place*
  * accumulate != 0 adds to the existing out (read in out_dt) before the epilogue.
  * bf16 operands whose dims fold to a (batched) matrix product run on MFMA; a one-operand einsum
  * that keeps every dim in place (a component-wise operation: scale, ReLU, mask) runs as a
- * vectorised pass; anything else runs on a generic fp32 FMA kernel.  b may be NULL (one-operand
- * einsum: component-wise operations, reductions, transposes).
+ * vectorised pass; anything else runs on fp32 FMAs (fp32 contractions that fold to a matrix product and
+ * fill its tiles through LDS, the rest one thread per output element; the same bits).  b may be NULL
+ * (one-operand einsum: component-wise operations, reductions, transposes).
  * Errors: NULL, RANK, DUP_DIM, SIZE_MISMATCH, OUT_NOT_SUBSET, ALIGN, UNSUPPORTED, HIP. */
 int mtf_einsum_local(const void* a, const mtf_shape* a_local, const void* b,
                      const mtf_shape* b_local, void* out, const mtf_shape* out_local,
@@ -179,14 +180,16 @@ int mtf_einsum_local_kranges(const void* a, const mtf_shape* a_local, const void
                              const mtf_shape* out_local, void* stream);
 
 /* Which kernel mtf_einsum_local would run for exactly these arguments: MTF_PATH_MFMA (the bf16
- * matrix-core kernel) or MTF_PATH_GENERIC (one thread per output element, fp32 FMA: the same
- * result up to summation order, one to two orders of magnitude slower at layer sizes), or the
- * negative status mtf_einsum_local would return.  The generic kernel takes over for fp32 inputs,
- * one-operand einsums, dim structures that do not fold to a (batched) matrix product, extents or
- * leading dims not divisible by 8 (odd leading dims), leading dims too large for the kernel's
- * 32-bit offsets, and a bias over an output dim that was merged with its neighbour.  Host only:
- * looks at shapes and addresses, launches nothing, needs no GPU. */
-#define MTF_PATH_GENERIC 0
+ * matrix-core kernel), MTF_PATH_COMPONENTWISE, or MTF_PATH_GENERIC (fp32 FMAs: the same result up to
+ * summation order, one to two orders of magnitude slower at layer sizes), or the negative status
+ * mtf_einsum_local would return.  MTF_PATH_GENERIC is all fp32 inputs with two operands (those that
+ * fold to a (batched) matrix product and fill 16x16 or 64x64 tiles run through LDS, bit for bit what
+ * one thread per output element gives, which is how everything else here runs), one-operand
+ * einsums that move or reduce dims, dim structures that do not fold, bf16 extents or leading dims not
+ * divisible by 8 (odd leading dims), leading dims too large for the matrix-core kernel's 32-bit
+ * offsets, and a bf16 bias over an output dim that was merged with its neighbour.  Host only: looks at
+ * shapes and addresses, launches nothing, needs no GPU. */
+#define MTF_PATH_GENERIC 0 /* fp32 FMAs */
 #define MTF_PATH_MFMA 1
 #define MTF_PATH_COMPONENTWISE 2 /* one operand, every dim kept in place: a vectorised HBM-bound pass */
 int mtf_einsum_local_path(const void* a, const mtf_shape* a_local, const void* b,

@@ -369,7 +369,8 @@ __device__ __forceinline__ void negate_slab(char* slab, int lane) {
   }
 }
 
-// One workgroup: NWAVES*32 query rows of one (batch, head); each wave owns 32 of them.
+// One workgroup: NWAVES / KVS * 32 query rows of one (batch, head); each wave owns 32 of them, the KVS
+// waves at the same place in their groups the same 32.
 template <int HD, int NWAVES, bool PAD = false, int KVS = 1>
 __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, false, KVS>::kWavesPerSimd)) attn_fwd_kernel(AttnArgs a) {
   using G = Geo<HD>;
@@ -607,7 +608,7 @@ __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, false
 }
 
 // ------------------------------------------------------------------------------------ backward
-// dq: one workgroup per NWAVES*32 query rows; loops over memory tiles.  Also produces
+// dq: one workgroup per NWAVES / KVS * 32 query rows; loops over memory tiles.  Also produces
 // delta[b,h,l] = sum_d dctx[b,l,h,d] * ctx[b,l,h,d] (= sum_m p * dp of the softmax Jacobian) for
 // its rows, which the dk/dv kernel launched after it reads.
 template <int HD, int NWAVES, bool PAD = false, int KVS = 1>
@@ -820,7 +821,7 @@ __global__ void __launch_bounds__(NWAVES * 64, (RowKernelShape<HD, NWAVES, HD ==
   store_rows_bf16<HD, PAD>(a.out0 + head0, rs, q0w, L, dq, 1.f, slab, lane, chunks);
 }
 
-// dk, dv: one workgroup per NWAVES*32 memory rows; loops over query tiles.  DK / DV select which of
+// dk, dv: one workgroup per NWAVES / KVS * 32 memory rows; loops over query tiles.  DK / DV select which of
 // the two gradients a launch produces: both at head width 128; at 256 one launch each (a wave
 // cannot hold its K and V fragments and both accumulator sets), each recomputing the
 // probabilities it needs.

@@ -89,7 +89,7 @@ def test_attention_core_negative_and_zero_scale(mtf, dk, scale):
 
 
 def test_attention_core_errors(mtf):
-    q = torch.zeros((1, 12, 2, 64), dtype=torch.bfloat16, device="cuda")     # length % 8 != 0, unfused path
+    q = torch.zeros((1, 12, 2, 64), dtype=torch.bfloat16, device="cuda")     # length % 8 != 0 at a width other than 128, 256
     with pytest.raises(mtf.MtfError) as e:
         mtf.attention_fwd(q, q, q, 1.0, False)
     assert e.value.name == "MTF_ERR_UNSUPPORTED"

@@ -213,7 +213,7 @@ def test_layer_config5_full_size():
 
 def test_rejected_shapes():
     x = torch.zeros(1, 8, 64, dtype=torch.bfloat16, device="cuda")
-    wq = torch.zeros(64, 2, 64, dtype=torch.bfloat16, device="cuda")           # d_k = 64: no fused kernel
+    wq = torch.zeros(64, 2, 64, dtype=torch.bfloat16, device="cuda")           # d_k = 64: the step takes 128 and 256
     wo = torch.zeros(2, 64, 64, dtype=torch.bfloat16, device="cuda")
     with pytest.raises(mtf.MtfError) as e:
         mtf.mha_fwd(x, wq, wq, wq, wo, 1.0, False)
