@@ -351,10 +351,10 @@ int mtf_layer_norm_bwd(const void* x, const void* gain, const void* mean, const 
   const int d = (int)d_model;
   int groups = 0;
   if (rows > 0) {
-    LaunchTimer timer("layer_norm_bwd_kernel", 0, (double)rows * d * 6.0 + 8.0 * rows + (double)bwd_groups(rows) * 2 * d * 4, s);
     auto go = [&](auto nc) {
       using S = BwdShape<decltype(nc)::value>;
       groups = (int)std::min<int64_t>(ceil_div(rows, S::kW), S::kMaxGroups);
+      LaunchTimer timer("layer_norm_bwd_kernel", 0, (double)rows * d * 6.0 + 8.0 * rows + (double)groups * 2 * d * 4, s);
       layer_norm_bwd_kernel<decltype(nc)::value><<<groups, S::kW * 64, 0, s>>>(
           static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(gain), static_cast<const float*>(mean),
           static_cast<const float*>(rstd), static_cast<const bf16_t*>(dy), rows, d, static_cast<bf16_t*>(dx),

@@ -31,6 +31,18 @@ def test_layer_norm_gradients(rows, d):
     assert ((dgain.double().cpu() - (dy.double() * xh).sum(0)).abs() <= (rows + 8) * 2.0**-24 * terms + 1e-30).all()
 
 
+@pytest.mark.parametrize("rows,d,groups", [(4096, 1024, 256), (33, 520, 5), (4096, 2048, 512), (33, 2048, 9)])
+def test_layer_norm_backward_reports_its_bytes(rows, d, groups):
+    """x, dy in and dx out in bf16, two fp32 statistics per row, the column partials of its workgroups."""
+    x = _ints((rows, d), 1).bfloat16().cuda()
+    _, mean, rstd = mtf.layer_norm_fwd(x, x[0], x[0], 1e-6)
+    mtf.timing_enable(True)
+    mtf.layer_norm_bwd(x, x[0], mean, rstd, x)
+    got = {t["kernel"]: t["bytes"] for t in mtf.timing_collect()}
+    mtf.timing_enable(False)
+    assert got["layer_norm_bwd_kernel"] == rows * d * 6 + 8 * rows + groups * 2 * d * 4
+
+
 @pytest.mark.parametrize("count", [0, 1, 127, 128, 129, 256, 257, 512, 513, 1023, 1024, 1025, 5000])
 @pytest.mark.parametrize("d", [8, 1024, 1032])
 def test_embedding_gradient_exact(count, d):
