@@ -163,7 +163,7 @@ def test_argument_validation_needs_no_gpu():
     assert lib.mtf_reduce_local(p, C.byref(big), p, C.byref(small), 0, 0, 0, None, C.c_size_t(0), None) == -11
     assert lib.mtf_reduce_local_workspace_bytes(C.byref(big), C.byref(small)) > 0
     # attention core at any head width
-    m64 = mtf.mtf_mha_dims(2, 16, 128, 2, 64)                                 # no fused kernel at this width
+    m64 = mtf.mtf_mha_dims(2, 16, 128, 2, 64)                                 # the unfused formulation's workspace, whichever runs
     assert lib.mtf_attention_fwd_workspace_bytes(C.byref(m64)) > 0
     for fused in (128, 256):
         mf = mtf.mtf_mha_dims(2, 16, 2 * fused, 2, fused)
